@@ -347,6 +347,7 @@ struct FwdWs {
   void *Y0, *Y1;  // BF16 iterates (never aliasing the FP32 ones)
   void *Yt0, *Yt1;  // their transposes (n x m, BF16): the Gram's operands, contiguous in k
   void* eigh;
+  int64_t conv_slots;  // stop-test slots per matrix that conv holds
   float *scale, *conv, *resid, *rpart, *colsum, *rowmax, *fro2, *fpart, *coef, *rcoef, *F, *aux, *mlpout, *nrm, *y0, *y1;
   float* qr;   // QR completion scratch: 2 m per matrix
   float* qrc;  // blocked QR: projection coefficients, n x kQrBlock per matrix
@@ -391,7 +392,9 @@ FwdWs carve_fwd(void* base, const svdp_params* p, size_t* total, bool dc = true)
   w.G = c.take<float>(b * n * n);
   w.eigh = c.take_bytes(eigh_ws_bytes(b, n, p->max_sweeps));
   w.scale = c.take<float>(b);
-  w.conv = c.take<float>(2 * b * gemm_conv_slots(m, n, b));
+  // also for the n x n core of a tall matrix and the blocks of a split's basis
+  w.conv_slots = gemm_conv_slots_max(m, n);
+  w.conv = c.take<float>(2 * b * w.conv_slots);
   w.resid = c.take<float>(b);
   w.rpart = c.take<float>(residual_part_floats(b));
   w.colsum = c.take<float>(b * n);
@@ -467,9 +470,9 @@ svdp_status read_counter(Ctx& c, const int* dev, int* out) {
   return SVDP_OK;
 }
 
-// One CANS step on buffers (Xc -> Xn): G = Xc^T Xc, Xn = alpha Xc + beta Xc G.
-// With ksched, matrix b takes part only if its step kidx has category kcat
-// (sched_cat over the per-matrix counts (K, K1)).
+// the change sums of an m x n update fit the workspace's buffer
+bool conv_fits(const Ctx& c) { return gemm_conv_slots(c.m, c.n, c.batch) <= c.w.conv_slots; }
+
 // One CANS step on buffers (Xc -> Xn): G = Xc^T Xc, Xn = alpha Xc + beta Xc G.
 // With ksched (the bounded schedule), matrix b takes part only if the
 // category of its step kidx is in kcatmask, and its output goes to Xn_bf
@@ -481,6 +484,7 @@ hipError_t cans_step(Ctx& c, int prec, const void* Xc, void* Xn, int in_bf16, in
                      float* conv, const StopTest* stop = nullptr, const int* ksched = nullptr, int kcatmask = 0, int obf_catmask = 0,
                      int kbf16 = 0, const void* Xtc = nullptr, void* Xn_bf = nullptr, void* Xtn = nullptr) {
   const int m = c.m, n = c.n, B = c.batch;
+  if (conv && !conv_fits(c)) return hipErrorInvalidValue;
   GemmArgs g = gemm_base(n, n, m, B);
   g.C = c.w.G; g.ldc = n; g.sC = (int64_t)n * n;
   g.sym = 1;
@@ -543,6 +547,7 @@ hipError_t stop_next(const Ctx& c, StopTest& s, int k, bool last) {
 hipError_t cans5_step(Ctx& c, const float* Xc, float* Xn, const double* cf, const int* active, float* conv,
                       const StopTest* stop = nullptr) {
   const int m = c.m, n = c.n, B = c.batch;
+  if (conv && !conv_fits(c)) return hipErrorInvalidValue;
   GemmArgs g = gemm_base(n, n, m, B);
   g.A = Xc; g.lda = n; g.sA = (int64_t)m * n;
   g.B = Xc; g.ldb = n; g.sB = (int64_t)m * n;

@@ -95,6 +95,10 @@ enum { PREC_F32 = 0, PREC_BF16 = 1 };
 hipError_t gemm_launch(const GemmArgs& g, int prec, int ta, int tb, hipStream_t st);
 // slots per matrix of GemmArgs::conv for an M x N output (one per wave sub-tile)
 int gemm_conv_slots(int64_t M, int64_t N, int64_t batch);
+// a bound on them for every output of at most M x N, M >= N (one slot per 32 x 32
+// block): the tile, and with it the count, depends on the shape, so that a
+// smaller output can need more slots (1 x 4096 x 2048: 2048, 1 x 2048^2: 4096)
+int64_t gemm_conv_slots_max(int64_t M, int64_t N);
 
 // Category of step k of matrix b in the bounded CANS schedule, from its step
 // counts (K, K1): K steps in all, the first K1 in FP32 (all of them when

@@ -57,6 +57,23 @@ def _ws(p, op):
     return st, out.value
 
 
+# The stop test's sums of one CANS iteration lie in a buffer sized for the call's
+# m x n; the n x n core of a tall matrix and an n x k block of a divide and
+# conquer basis iterate in the same workspace, with a tile and so a count of their own.
+@pytest.mark.parametrize("b", [1, 2, 3, 5, 8, 12, 33, 256])
+def test_stop_test_slots_fit(b):
+    _, lib = _lib()
+    slots, cap = lib._Z15gemm_conv_slotslll, lib._Z19gemm_conv_slots_maxll
+    slots.argtypes, slots.restype = [ctypes.c_int64] * 3, ctypes.c_int
+    cap.argtypes, cap.restype = [ctypes.c_int64] * 2, ctypes.c_int64
+    sizes = [1, 31, 33, 64, 65, 127, 129, 512, 640, 1290, 1536, 1792, 2048, 3456, 4225, 8192]
+    for n in sizes:
+        for f in (1.0, 1.01, 2.0, 2.5, 3.0):
+            m = int(np.ceil(f * n))
+            for mm, nn in [(m, n), (n, n), (m, max(n - 1, 1)), (m, (n + 1) // 2), (n, 1)]:
+                assert 0 < slots(mm, nn, b) <= cap(m, n), (b, m, n, mm, nn)
+
+
 def test_workspace_size_and_shape_validation():
     L, _ = _lib()
     st, nb = _ws(L.default_params(256, 512, 512), L.OP_SVD_FWD)

@@ -172,3 +172,29 @@ def test_tall_qr_blocks(api, m, n):
         assert torch.linalg.norm(U[i].T @ U[i] - eye, 2) <= tol
         assert torch.linalg.norm(V[i].T @ V[i] - eye, 2) <= tol
         assert torch.linalg.norm((U[i] * S[i]) @ V[i].T - A[i], 2) <= tol * ref[i, 0]
+
+
+# above 1024 columns the n x n core takes 64-wide tiles where the tall matrix
+# takes 128-wide ones: twice the stop test's slots (4 x 3072 x 1536, 1 x 4096 x 2048)
+@pytest.mark.parametrize("b,m,n", [(1, 4096, 2048), (4, 3072, 1536), (5, 2580, 1290)])
+def test_tall_core_slots(api, b, m, n):
+    import torch
+    print(f"tall core {b} x {m} x {n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m)
+
+    def orth(r, c):
+        return torch.linalg.qr(torch.randn(r, c, generator=g, device="cuda", dtype=torch.float64))[0]
+
+    s = torch.linspace(1.0, 0.1, n, device="cuda", dtype=torch.float64)
+    A = torch.stack([(orth(m, n) * s) @ orth(n, n).T for _ in range(b)]).float()
+    U, S, V, info = api.svd_fwd(A)
+    assert (api.info_to_numpy(info)["flags"] & (FAILED | 1) == 0).all()
+    tol = 32 * EPS * np.sqrt(n)
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    for i in range(b):
+        u, v = U[i].double(), V[i].double()
+        assert (S[i].double() - s).abs().max() <= tol
+        # Frobenius against sqrt(n) times the 2-norm bound
+        assert torch.linalg.norm(u.T @ u - eye) <= tol * np.sqrt(n)
+        assert torch.linalg.norm(v.T @ v - eye) <= tol * np.sqrt(n)
+        assert torch.linalg.norm((u * S[i].double()) @ v.T - A[i].double()) <= tol * np.sqrt(n)
