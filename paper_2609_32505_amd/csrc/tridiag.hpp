@@ -21,7 +21,7 @@ struct TriWs {
   double* zinv;      // batch x np: 1 / |column of Z|
   float* tau;        // batch x np: the reflectors' factors
   float* T;          // batch x tri_t_floats(np): compact-WY factors, one per panel
-  double* lam;       // batch x np: eigenvalues of the perturbed T, ascending
+  double* lam;       // batch x np: eigenvalues of the perturbed T, ascending, up to a shift (k_tri_vectors)
   float* mx;         // batch x (np / 64)^2: max |h_ij| per setup workgroup
   float *S, *T4, *C;  // np > kTriSlab, batch x np x 128 each: Gram matrices and WY factors of 128
                      // reflectors, and 128 rows of products

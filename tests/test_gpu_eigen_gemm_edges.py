@@ -51,6 +51,34 @@ def test_eigh_edges(api, n, kind):
         assert np.linalg.norm((V[i] * lam[i]) @ V[i].T - M, 2) <= tol * scale
 
 
+# Spectra that are narrow beside their distance from zero: the Gram matrix of a
+# matrix that is orthonormal to FP32 rounding, and I + noise of FP32 rounding size,
+# both signs.  Eigenvectors resolved against the offset are orthonormal to 1e-4 only.
+@pytest.mark.parametrize("b,n", [(64, 128), (48, 300), (24, 512), (4, 1024)])
+@pytest.mark.parametrize("kind", ["gram", "noise", "negative"])
+def test_eigh_narrow_spectrum(api, b, n, kind):
+    import torch
+    print(f"narrow spectrum {kind} {b} x {n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(7 * n + len(kind))
+    N = torch.randn(b, n, n, generator=g, device="cuda", dtype=torch.float64)
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    if kind == "gram":
+        Q = torch.linalg.qr(N)[0].float().double()
+        H = Q.transpose(1, 2).contiguous() @ Q
+    else:
+        H = eye + 1e-7 / np.sqrt(n) * (N + N.transpose(1, 2))
+    if kind == "negative":
+        H = -H
+    H = H.float()
+    lam, V, info = api.eigh(H)
+    assert (api.info_to_numpy(info)["flags"] & FAILED == 0).all()
+    V, lam, H = V.double(), lam.double(), H.double()
+    tol = 8 * EPS * np.sqrt(n) + 16 * EPS
+    # per entry: the 2-norm bound holds for each
+    assert float((V.transpose(1, 2).contiguous() @ V - eye).abs().max()) <= tol
+    assert float(((V * lam[:, None, :]) @ V.transpose(1, 2).contiguous() - H).abs().max()) <= tol
+
+
 def test_eigh_nan_is_flagged_alone(api):
     import torch
     H = torch.randn(3, 70, 70, generator=torch.Generator().manual_seed(5))
