@@ -964,6 +964,7 @@ svdp_status svd_tail(Ctx& c, float* U, int64_t ldu, int64_t sU, float* S, int64_
     HIPCHK(eigh_run(e, w.G, n, (int64_t)n * n, 1, opts, S, sS, V, ldv, sV, w.sweeps, w.flags, mask, &c.h->aux, c.st),
            "eigh");
     if (rescue && (s = read_counter(c, e.tri.bad, &bad))) return s;
+    bad = rescue && bad > 1;
   }
   if (bad) {
     // one large FP32 matrix: H = V diag(lam) V^T by divide and conquer, then

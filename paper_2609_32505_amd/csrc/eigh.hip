@@ -44,7 +44,6 @@
 #include <vector>
 #include "common.hpp"
 #include "eigh.hpp"
-#include "kernels.hpp"
 #include "prof.hpp"
 #include "tridiag_kernels.hpp"
 
@@ -1162,8 +1161,8 @@ static hipError_t sort_launch(const EighWs& e, const float* lsrc, int64_t sl, in
 }
 
 // The tridiagonal route: V = Q Z (tri_eig); matrices with eigenvalues that
-// nearly coincide get one Newton-Schulz step, V2 = V (3 I - V^T V) / 2 (and a
-// Jacobi run where V is far from orthonormal); then the eigenvalues as Rayleigh
+// nearly coincide get one Newton-Schulz step, V2 = V (3 I - V^T V) / 2 (after
+// tri_rescue where V is further from orthonormal than that mends); then the eigenvalues as Rayleigh
 // quotients with the input, or all of T = V^T H V where it is wanted.  The backward
 // error is 0.5 to 2e-6 |H|_F from n = 24 to 1024, below any useful
 // eigh_off_tol, so nothing is swept again.
@@ -1179,11 +1178,8 @@ static hipError_t eigh_tri_run(const EighWs& e, const float* H, int64_t ldh, int
   g.sym = 1;
   if ((err = gemm_launch(g, PREC_F32, 1, 0, st))) return err;
   if ((err = tri_check(t, e.Hw, mask, st))) return err;
-  // above kTriSlab one workgroup would take minutes: the matrix is flagged where
-  // the caller has no other solver for it
-  if (np <= kTriSlab) err = tri_rescue(t, H, ldh, sH, mask, st);
-  else if (!o.rescued) err = or_flags_launch(batch, flags, SVDP_FLAG_EIGH_NOT_CONVERGED, t.bad, st);
-  if (err) return err;
+  // a matrix whose vectors stay bad is flagged where the caller has no other solver for it
+  if ((err = tri_rescue(t, e.Hw, o.rescued ? nullptr : flags, mask, st))) return err;
   g.active = t.bad;
   if ((err = gemm_launch(g, PREC_F32, 1, 0, st))) return err;
   GemmArgs u = square_product(n, batch, t.V, np, m2, e.Hw, np, m2, e.V2, np, m2, t.risk);

@@ -70,7 +70,7 @@ struct EighOpts {
   float neg_tol;     // NEG_EIGENVALUE when lam_min < -neg_tol max|lam| (mode 1)
   float off_tol;     // restarts end once |off(V^T H V)|_F <= off_tol |H|_F
   int restarts;      // cap on restarts (re-formed V^T H V swept again from I)
-  bool rescued;      // the caller solves matrices of TriWs::bad again (np > kTriSlab)
+  bool rescued;      // the caller solves matrices of TriWs::bad = 2 again, which are not flagged
   bool need_t;       // V^T H V is wanted in Vw (the BF16 correction reads it)
 };
 

@@ -27,7 +27,7 @@ struct TriWs {
                      // reflectors, and 128 rows of products
   float* Y;          // np > kTriSlab, batch x np x np: T4^T V^T (may overlay Zb behind V)
   int* risk;         // batch: 1 where eigenvalues nearly coincide
-  int* bad;          // batch: 1 where V is not orthonormal
+  int* bad;          // batch: 1 where V was not orthonormal, 2 where it still is not
 };
 
 // In tridiag_kernels.hpp:
@@ -37,4 +37,6 @@ struct TriWs {
 // other memory that is free by then, V may overlay Zb.
 // tri_check: bad[b] = 1 where max |G - I| > 1e-4 for the Gram matrix G of V,
 // among those of risk.
-// tri_rescue: plain cyclic Jacobi for the matrices of bad (A, V overwritten).
+// tri_rescue: the vectors of close eigenvalues orthogonalised for the matrices of
+// bad, which is 2 (and flags[b] |= EIGH_NOT_CONVERGED, unless flags is null) where
+// they were too many.

@@ -1048,7 +1048,7 @@ __global__ __launch_bounds__(64 * W, TPW <= 2 ? 3 : 2) void k_tri_back(TriWs t, 
 }
 
 // bad[b] = 1 where some |G - I| entry is above 1e-4: one Newton-Schulz step
-// then leaves more than FP32 rounding
+// alone would leave more than FP32 rounding
 __global__ __launch_bounds__(256) void k_tri_dev(TriWs t, const float* G, const int* mask) {
   const int b = blockIdx.y;
   if ((mask && !mask[b]) || !t.risk[b]) return;
@@ -1060,10 +1060,6 @@ __global__ __launch_bounds__(256) void k_tri_dev(TriWs t, const float* G, const 
   if ((threadIdx.x & 63) == 0 && m > 1e-4f && isfinite(m)) t.bad[b] = 1;
 }
 
-// Plain cyclic Jacobi (round-robin pairs) for a matrix whose vectors failed
-// the orthonormality test: slow, one workgroup per matrix, and reached only by
-// matrices built to have eigenvalues that agree beyond FP64 after the
-// perturbation.  A and V in global memory.
 // lam_k = v_k^T (H v_k), Y = H V, summed in FP64: a wave takes every blockDim /
 // 64-th row of 64 columns.  Bound by reading V and Y once (256 x 512^2: 104 us,
 // where the full product V^T Y took 500; 4096^2: 42 for 772, and its FP32 sums of
@@ -1148,88 +1144,152 @@ __global__ __launch_bounds__(256) void k_tri_merge(TriWs t) {
   for (int q = tid; q < 128 * 128; q += 256) Tg[q] = T[(q >> 7) * 129 + (q & 127)];
 }
 
-__global__ __launch_bounds__(1024) void k_tri_rescue(TriWs t, const float* Hin, int64_t ldh, int64_t sH,
-                                                     const int* mask) {
+// Orthogonalises the columns of V whose entries of the Gram matrix G are above
+// 3e-5 (eigenvalues that agree to 1e-11 or so of their size, where FP64 leaves
+// eps |lam| / gap), one workgroup per matrix of bad; what is left is a
+// Newton-Schulz step's.  Columns ascend by eigenvalue, so such columns are
+// neighbours: a cluster is a run of columns bridged by large entries, and within
+// it column j loses its components along the earlier ones, which mixes vectors
+// of eigenvalues that differ by less than FP32 resolves.  A column that keeps less
+// than 0.3 of itself (FP64 gave the same vector twice) is replaced in the end by a
+// random one with the components along every other column taken off: those
+// leave it the rest of the same eigenspace.  Latency bounds it: a pair takes a sum
+// over the workgroup, a replacement three passes over V.  Above kTriSlab, more than
+// 128 n pairs or 2^34 / n^2 replacements (seconds) end it: bad = 2, and the matrix
+// is flagged when flags is given.
+__global__ __launch_bounds__(1024) void k_tri_rescue(TriWs t, const float* G, int* flags, const int* mask) {
   const int b = blockIdx.x;
   if ((mask && !mask[b]) || !t.bad[b]) return;
-  __shared__ float cs[kTriSlab / 2], sn[kTriSlab / 2];
-  __shared__ int big;
-  __shared__ float hmax[16];
-  const int n = t.n, tid = threadIdx.x;
+  constexpr int PER = kTriMax / 1024;
+  __shared__ int start[kTriMax];  // a row's first large entry, then its cluster's first column
+  __shared__ unsigned char lost[kTriMax];
+  __shared__ double part[2][16];
+  extern __shared__ __attribute__((aligned(16))) double xy[];  // n and n
+  const int n = t.n, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int64_t ld = t.np;
-  float* A = t.A + (int64_t)b * ld * ld;
+  double *x = xy, *y = xy + n;
   float* V = t.V + (int64_t)b * ld * ld;
-  const float* Hb = Hin + b * sH;
-  float m = 0.f;
-  for (int i = 0; i < n; ++i)
-    for (int j = tid; j < n; j += 1024) {
-      const float v = 0.5f * Hb[(int64_t)i * ldh + j] + 0.5f * Hb[(int64_t)j * ldh + i];
-      A[(int64_t)i * ld + j] = v;
-      V[(int64_t)i * ld + j] = i == j ? 1.f : 0.f;
-      m = fmaxf(m, fabsf(v));
-    }
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((tid & 63) == 0) hmax[tid >> 6] = m;
+  const float* Gb = G + (int64_t)b * ld * ld;
+  for (int j = w; j < n; j += 16) {
+    int first = j;
+    for (int i = lane; i < j; i += 64)
+      if (fabsf(Gb[(int64_t)j * ld + i]) > 3e-5f) first = min(first, i);
+    for (int off = 32; off > 0; off >>= 1) first = min(first, __shfl_xor(first, off));
+    if (lane == 0) start[j] = first;
+  }
+  for (int j = tid; j < n; j += 1024) lost[j] = 0;
   __syncthreads();
-  for (int i = 0; i < 16; ++i) m = fmaxf(m, hmax[i]);
-  const float floor_abs = 3e-8f * m;
-  const int N = (n + 1) & ~1, np2 = N / 2;
-  for (int sweep = 0; sweep < 30; ++sweep) {
-    if (tid == 0) big = 0;
-    __syncthreads();
-    for (int round = 0; round < N - 1; ++round) {
-      // circle method: player N - 1 stays, the others rotate
-      auto pair_of = [&](int k, int& p, int& q) {
-        p = k == 0 ? N - 1 : (round + k) % (N - 1);
-        q = k == 0 ? round : (round + N - 1 - k) % (N - 1);
-        if (p > q) { const int x = p; p = q; q = x; }
-      };
-      for (int k = tid; k < np2; k += 1024) {
-        int p, q;
-        pair_of(k, p, q);
-        float c = 1.f, s = 0.f;
-        if (q < n) {
-          const double app = A[(int64_t)p * ld + p], aqq = A[(int64_t)q * ld + q], apq = A[(int64_t)p * ld + q];
-          if (fabs(apq) > (double)floor_abs / n) {
-            const double tau = (aqq - app) / (2.0 * apq);
-            const double tt = (tau >= 0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = (float)(1.0 / sqrt(1.0 + tt * tt));
-            s = (float)(tt / sqrt(1.0 + tt * tt));
-            if (fabs(apq) > (double)floor_abs) big = 1;
-          }
-        }
-        cs[k] = c;
-        sn[k] = s;
-      }
-      __syncthreads();
-      for (int idx = tid; idx < np2 * n; idx += 1024) {
-        const int k = idx / n, j = idx - k * n;
-        int p, q;
-        pair_of(k, p, q);
-        if (q >= n || sn[k] == 0.f) continue;
-        const float x = A[(int64_t)p * ld + j], y = A[(int64_t)q * ld + j];
-        A[(int64_t)p * ld + j] = cs[k] * x - sn[k] * y;
-        A[(int64_t)q * ld + j] = sn[k] * x + cs[k] * y;
-      }
-      __syncthreads();
-      for (int idx = tid; idx < np2 * n; idx += 1024) {
-        const int i = idx / np2, k = idx - i * np2;
-        int p, q;
-        pair_of(k, p, q);
-        if (q >= n || sn[k] == 0.f) continue;
-        float x = A[(int64_t)i * ld + p], y = A[(int64_t)i * ld + q];
-        A[(int64_t)i * ld + p] = cs[k] * x - sn[k] * y;
-        A[(int64_t)i * ld + q] = sn[k] * x + cs[k] * y;
-        x = V[(int64_t)i * ld + p];
-        y = V[(int64_t)i * ld + q];
-        V[(int64_t)i * ld + p] = cs[k] * x - sn[k] * y;
-        V[(int64_t)i * ld + q] = sn[k] * x + cs[k] * y;
-      }
-      __syncthreads();
+  if (tid == 0) {
+    // columns j - 1 and j are bridged if some row from j on reaches before j
+    int reach = n;
+    for (int j = n - 1; j >= 0; --j) {
+      reach = min(reach, start[j]);
+      start[j] = reach < j ? -1 : j;
     }
-    const int more = big;
+    for (int j = 1; j < n; ++j)
+      if (start[j] < 0) start[j] = start[j - 1];
+  }
+  __syncthreads();
+  int par = 0;
+  auto total = [&](double x) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+    par ^= 1;
+    if (lane == 0) part[par][w] = x;
     __syncthreads();
-    if (!more) break;
+    x = 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) x += part[par][q];
+    return x;
+  };
+  double v[PER];
+  // v loses its component along column i
+  auto take_off = [&](int i) {
+    double c[PER], s = 0.0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int r = tid + 1024 * u;
+      c[u] = r < n ? (double)V[(int64_t)r * ld + i] : 0.0;
+      s = fma(c[u], v[u], s);
+    }
+    s = total(s);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) v[u] = fma(-s, c[u], v[u]);
+  };
+  auto store = [&](int j, double scale) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int r = tid + 1024 * u;
+      if (r < n) V[(int64_t)r * ld + j] = (float)(v[u] * scale);
+    }
+  };
+  auto norm2 = [&] {
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) s = fma(v[u], v[u], s);
+    return total(s);
+  };
+  const bool bounded = n > kTriSlab;
+  int64_t budget = bounded ? 128 * n : INT64_MAX;  // pairs
+  int dropped = 0;
+  for (int j = 1; j < n && budget > 0; ++j) {
+    if (start[j] == j) continue;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int r = tid + 1024 * u;
+      v[u] = r < n ? (double)V[(int64_t)r * ld + j] : 0.0;
+    }
+    for (int i = start[j]; i < j; ++i)
+      if (!lost[i]) {
+        take_off(i);
+        --budget;
+      }
+    const double s = norm2();
+    const bool drop = s < 0.09;
+    store(j, drop ? 0.0 : 1.0 / sqrt(s));
+    if (tid == 0) lost[j] = drop;
+    dropped += drop;
+    __syncthreads();
+  }
+  if (bounded && (int64_t)dropped * n * n > int64_t(1) << 34) budget = 0;
+  for (int j = 1; dropped && j < n && budget > 0; ++j) {
+    if (!lost[j]) continue;
+    for (int r = tid; r < n; r += 1024) {
+      unsigned h = (unsigned)(r * 4096 + j) * 2654435761u + 974711u;
+      h = (h ^ (h >> 15)) * 2246822519u;
+      h = (h ^ (h >> 13)) * 3266489917u;
+      x[r] = (double)(int)(h ^ (h >> 16)) * (1.0 / 2147483648.0);
+    }
+    for (int pass = 0; pass < 3; ++pass) {  // x -= V (V^T x); lost columns are zero
+      __syncthreads();
+      for (int i = tid; i < n; i += 1024) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int r = 0; r < n; ++r) s = fma((double)V[(int64_t)r * ld + i], x[r], s);
+        y[i] = s;
+      }
+      __syncthreads();
+      for (int r = w; r < n; r += 16) {
+        double s = 0.0;
+        for (int i = lane; i < n; i += 64) s = fma((double)V[(int64_t)r * ld + i], y[i], s);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        if (lane == 0) x[r] -= s;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int r = tid + 1024 * u;
+      v[u] = r < n ? x[r] : 0.0;
+    }
+    const double s = norm2();
+    store(j, 1.0 / sqrt(s));
+    __syncthreads();
+  }
+  if (budget <= 0 && tid == 0) {
+    t.bad[b] = 2;
+    if (flags) atomicOr(flags + b, 32);  // SVDP_FLAG_EIGH_NOT_CONVERGED
   }
 }
 
@@ -1364,8 +1424,7 @@ static hipError_t tri_rayleigh(const TriWs& t, const float* V2, const float* Y, 
   return hipGetLastError();
 }
 
-static hipError_t tri_rescue(const TriWs& t, const float* H, int64_t ldh, int64_t sH, const int* mask, hipStream_t st) {
-  if (t.np > kTriSlab) return hipSuccess;
-  hipLaunchKernelGGL(k_tri_rescue, dim3(t.batch), dim3(1024), 0, st, t, H, ldh, sH, mask);
+static hipError_t tri_rescue(const TriWs& t, const float* G, int* flags, const int* mask, hipStream_t st) {
+  hipLaunchKernelGGL(k_tri_rescue, dim3(t.batch), dim3(1024), (size_t)t.n * 16, st, t, G, flags, mask);
   return hipGetLastError();
 }

@@ -79,6 +79,62 @@ def test_eigh_narrow_spectrum(api, b, n, kind):
     assert float(((V * lam[:, None, :]) @ V.transpose(1, 2).contiguous() - H).abs().max()) <= tol
 
 
+def _ties(n, offset):
+    """diag(1, d_i + offset) with d_i + the route's perturbation of entry i equal for
+    all i: eigenvalues that FP64 does not tell apart, whose vectors come out the same."""
+    i = np.arange(n, dtype=np.uint64)
+    h = ((i * 40503) & 0xffff) / 65536.0 - 0.5
+    d = (offset - h) * 2.0 ** -25
+    d[0] = 1.0
+    return np.diag(d).astype(np.float32)
+
+
+@pytest.mark.parametrize("n", [3, 65, 130, 300])
+def test_eigh_coinciding_eigenvalues(api, n):
+    import torch
+    print(f"ties n={n}", flush=True)
+    H = _ties(n, 0.0)
+    lam, V, info = api.eigh(torch.from_numpy(np.stack([H, np.eye(n, dtype=np.float32)])).cuda())
+    assert (api.info_to_numpy(info)["flags"] & FAILED == 0).all()
+    lam, v = lam[0].cpu().double().numpy(), V[0].cpu().double().numpy()
+    tol = 8 * EPS * np.sqrt(n) + 16 * EPS
+    assert np.linalg.norm(v.T @ v - np.eye(n), 2) <= tol
+    assert np.linalg.norm((v * lam) @ v.T - H, 2) <= tol
+
+
+# above 1024, where nothing but these vectors' own orthogonalisation solves a batch:
+# ties, half the values 1 and half 1/2, and rank 3 (W of the null space is arbitrary)
+@pytest.mark.parametrize("n,kind", [(1100, "ties"), (2000, "halves"), (1100, "rank3"), (2300, "ties")])
+def test_polar_close_eigenvalues_large(api, n, kind):
+    import torch
+    print(f"polar close eigenvalues {kind} n={n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    if kind == "ties":
+        A = torch.from_numpy(_ties(n, 1.0)).cuda().expand(2, n, n).contiguous()
+    else:
+        Q = [torch.linalg.qr(torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64))[0] for _ in range(4)]
+        s = torch.ones(n, device="cuda", dtype=torch.float64)
+        s[n // 2 if kind == "halves" else 3:] = 0.5 if kind == "halves" else 0.0
+        A = torch.stack([(Q[2 * i] * s) @ Q[2 * i + 1] for i in range(2)]).float()
+    W, H, S, V, info = api.polar_fwd(A, cache=True)
+    assert (api.info_to_numpy(info)["flags"] & FAILED == 0).all()
+    tol = 8 * EPS * np.sqrt(n) + 16 * EPS
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    for i in range(2):
+        v, lam = V[i].double(), S[i].double()
+        # Frobenius against sqrt(n) times the 2-norm bound
+        assert float(torch.linalg.norm(v.T @ v - eye)) <= tol * np.sqrt(n)
+        assert float(torch.linalg.norm((v * lam) @ v.T - H[i].double())) <= tol * np.sqrt(n)
+    if kind != "halves":
+        return
+    # the gradient does not depend on the basis within an eigenspace: polar_bwd's own
+    # eigendecomposition against the given one
+    dH = torch.randn(2, n, n, generator=g, device="cuda")
+    dA = api.polar_bwd(A, H, dH=dH)
+    ref = api.polar_bwd(A, H, S=S, V=V, dH=dH)
+    assert float((dA - ref).abs().max()) <= 16 * tol * float(ref.abs().max())
+
+
 def test_eigh_nan_is_flagged_alone(api):
     import torch
     H = torch.randn(3, 70, 70, generator=torch.Generator().manual_seed(5))
