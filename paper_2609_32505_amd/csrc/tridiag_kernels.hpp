@@ -1155,7 +1155,7 @@ __global__ __launch_bounds__(256) void k_tri_merge(TriWs t) {
 // random one with the components along every other column taken off: those
 // leave it the rest of the same eigenspace.  Latency bounds it: a pair takes a sum
 // over the workgroup, a replacement three passes over V.  Above kTriSlab, more than
-// 128 n pairs or 2^34 / n^2 replacements (seconds) end it: bad = 2, and the matrix
+// 128 n pairs or 2^32 / n^2 replacements (seconds) end it: bad = 2, and the matrix
 // is flagged when flags is given.
 __global__ __launch_bounds__(1024) void k_tri_rescue(TriWs t, const float* G, int* flags, const int* mask) {
   const int b = blockIdx.x;
@@ -1251,7 +1251,7 @@ __global__ __launch_bounds__(1024) void k_tri_rescue(TriWs t, const float* G, in
     dropped += drop;
     __syncthreads();
   }
-  if (bounded && (int64_t)dropped * n * n > int64_t(1) << 34) budget = 0;
+  if (bounded && (int64_t)dropped * n * n > int64_t(1) << 32) budget = 0;
   for (int j = 1; dropped && j < n && budget > 0; ++j) {
     if (!lost[j]) continue;
     for (int r = tid; r < n; r += 1024) {

@@ -79,13 +79,16 @@ def test_eigh_narrow_spectrum(api, b, n, kind):
     assert float(((V * lam[:, None, :]) @ V.transpose(1, 2).contiguous() - H).abs().max()) <= tol
 
 
-def _ties(n, offset):
+def _ties(n, offset, count=None):
     """diag(1, d_i + offset) with d_i + the route's perturbation of entry i equal for
-    all i: eigenvalues that FP64 does not tell apart, whose vectors come out the same."""
+    the first count of them: eigenvalues that FP64 does not tell apart, whose vectors
+    come out the same.  The others are spread over (0.2, 0.9)."""
     i = np.arange(n, dtype=np.uint64)
     h = ((i * 40503) & 0xffff) / 65536.0 - 0.5
     d = (offset - h) * 2.0 ** -25
     d[0] = 1.0
+    if count is not None:
+        d[count:] = np.linspace(0.2, 0.9, n - count)
     return np.diag(d).astype(np.float32)
 
 
@@ -103,14 +106,15 @@ def test_eigh_coinciding_eigenvalues(api, n):
 
 
 # above 1024, where nothing but these vectors' own orthogonalisation solves a batch:
-# ties, half the values 1 and half 1/2, and rank 3 (W of the null space is arbitrary)
-@pytest.mark.parametrize("n,kind", [(1100, "ties"), (2000, "halves"), (1100, "rank3"), (2300, "ties")])
+# ties, a few of them, half the values 1 and half 1/2, and rank 3 (W of the null
+# space is arbitrary)
+@pytest.mark.parametrize("n,kind", [(1100, "ties"), (2000, "halves"), (1100, "rank3"), (2300, "some")])
 def test_polar_close_eigenvalues_large(api, n, kind):
     import torch
     print(f"polar close eigenvalues {kind} n={n}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(n)
-    if kind == "ties":
-        A = torch.from_numpy(_ties(n, 1.0)).cuda().expand(2, n, n).contiguous()
+    if kind in ("ties", "some"):
+        A = torch.from_numpy(_ties(n, 1.0, None if kind == "ties" else 150)).cuda().expand(2, n, n).contiguous()
     else:
         Q = [torch.linalg.qr(torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64))[0] for _ in range(4)]
         s = torch.ones(n, device="cuda", dtype=torch.float64)
@@ -133,6 +137,15 @@ def test_polar_close_eigenvalues_large(api, n, kind):
     dA = api.polar_bwd(A, H, dH=dH)
     ref = api.polar_bwd(A, H, S=S, V=V, dH=dH)
     assert float((dA - ref).abs().max()) <= 16 * tol * float(ref.abs().max())
+
+
+def test_too_many_coinciding_eigenvalues_are_flagged(api):
+    import torch
+    n = 2300
+    ok = torch.diag(torch.linspace(0.5, 1.0, n))
+    A = torch.stack([torch.from_numpy(_ties(n, 1.0)), ok]).cuda()
+    W, H, S, V, info = api.polar_fwd(A, cache=True)
+    assert list(api.info_to_numpy(info)["flags"] & FAILED) == [32, 0]
 
 
 def test_eigh_nan_is_flagged_alone(api):
