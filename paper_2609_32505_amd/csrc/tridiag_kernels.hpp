@@ -740,12 +740,12 @@ __global__ __launch_bounds__(64) void k_tri_vectors(TriWs t, const int* mask) {
     lo = fmin(lo, __shfl_xor(lo, off));
     hi = fmax(hi, __shfl_xor(hi, off));
   }
-  // A spectrum on one side of zero is moved to its nearer end: eigenvalues, and
-  // with them the vectors, are resolved to 2^-52 |lam|, which has to be small
-  // against the spectrum's width (the rule of `risk`), not its offset (H near a
-  // multiple of I: max |V^T V - I| 1.5e-5 with the offset, 3e-11 without).  One
-  // around zero stays, and so does the resolution of values near zero.
-  const double sh = lo > 0.0 ? lo : (hi < 0.0 ? hi : 0.0);
+  // A spectrum further from zero than it is wide is moved to that distance:
+  // eigenvalues, and with them the vectors, are resolved to 2^-52 |lam|, which has
+  // to be small against the spectrum's width (the rule of `risk`), not its offset
+  // (H near a multiple of I: max |V^T V - I| 1.5e-5 with the offset, 3e-11
+  // without).  Nearer to zero, values near it would take passes of their own.
+  const double wd = hi - lo, sh = lo > wd ? lo - wd : (hi < -wd ? hi + wd : 0.0);
   for (int i = lane; i < n; i += 64) de[2 * i] -= sh;
   __syncthreads();
   lo -= sh;
