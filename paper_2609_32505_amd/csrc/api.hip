@@ -879,8 +879,8 @@ svdp_status qr_blocks(Ctx& c, float* U, int64_t ldu, int64_t sU, const int* qmas
       g.sym = 1; g.active = qmask;
       HIPCHK(gemm_launch(g, PREC_F32, 1, 0, c.st), "qr gram");
       HIPCHK(qr_chol_launch(w.qrg, w.qrr, B, bc, qmask, zero_dep, c.st), "qr chol");
-      // in place: each workgroup reads the rows of U[:, blk] it writes, and
-      // K = bc is consumed before its epilogue
+      // in place: each workgroup reads the rows of U[:, blk] it writes (bc <= 64:
+      // one tile across), all of them before its epilogue
       GemmArgs r = gemm_base(m, bc, bc, B);  // U[:, blk] <- U[:, blk] Rinv
       r.A = U + c0; r.lda = ldu; r.sA = sU;
       r.B = w.qrr; r.ldb = bc; r.sB = (int64_t)kQrBlock * kQrBlock;

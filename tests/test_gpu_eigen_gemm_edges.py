@@ -295,3 +295,20 @@ def test_tall_core_slots(api, b, m, n):
         assert torch.linalg.norm(u.T @ u - eye) <= tol * np.sqrt(n)
         assert torch.linalg.norm(v.T @ v - eye) <= tol * np.sqrt(n)
         assert torch.linalg.norm((u * S[i].double()) @ v.T - A[i].double()) <= tol * np.sqrt(n)
+
+
+# the blocked QR scales its columns in place, also where a row holds an infinity
+# and the product takes its plain sums
+def test_tall_infinity_is_flagged_alone(api):
+    import torch
+    g = torch.Generator().manual_seed(11)
+    A = torch.randn(2, 300, 70, generator=g)
+    ref = api.svd_fwd(A.cuda())[1]
+    A[1, 5, 3] = float("inf")
+    out = [api.svd_fwd(A.cuda()) for _ in range(3)]
+    for U, S, V, info in out:
+        flags = api.info_to_numpy(info)["flags"]
+        assert list(flags & 16 != 0) == [False, True]
+        assert torch.equal(S[0], ref[0])
+        for x, y in zip((U, S, V), out[0]):
+            assert torch.equal(x.isnan(), y.isnan()) and torch.equal(x.nan_to_num(), y.nan_to_num())
