@@ -1160,12 +1160,12 @@ static hipError_t sort_launch(const EighWs& e, const float* lsrc, int64_t sl, in
   return hipGetLastError();
 }
 
-// The tridiagonal route: V = Q Z (tri_eig); matrices with eigenvalues that
-// nearly coincide get one Newton-Schulz step, V2 = V (3 I - V^T V) / 2 (after
-// tri_rescue where V is further from orthonormal than that mends); then the eigenvalues as Rayleigh
-// quotients with the input, or all of T = V^T H V where it is wanted.  The backward
-// error is 0.5 to 2e-6 |H|_F from n = 24 to 1024, below any useful
-// eigh_off_tol, so nothing is swept again.
+// The tridiagonal route: V = Q Z (tri_eig); matrices up to kTriPolish and those
+// with eigenvalues that nearly coincide get one Newton-Schulz step, V2 =
+// V (3 I - V^T V) / 2 (after tri_rescue where V is further from orthonormal than
+// that mends); then the eigenvalues as Rayleigh quotients with the input, or all
+// of T = V^T H V where it is wanted.  The backward error is 0.5 to 2e-6 |H|_F from
+// n = 24 to 1024, below any useful eigh_off_tol, so nothing is swept again.
 static hipError_t eigh_tri_run(const EighWs& e, const float* H, int64_t ldh, int64_t sH, int mode, const EighOpts& o,
                                float* lam, int64_t slam, float* Vout, int64_t ldv, int64_t sV, int* sweeps_out,
                                int* flags, const int* mask, hipStream_t st) {
@@ -1174,18 +1174,25 @@ static hipError_t eigh_tri_run(const EighWs& e, const float* H, int64_t ldh, int
   const int64_t m2 = (int64_t)np * np;
   const TriWs& t = e.tri;
   if ((err = tri_eig(t, H, ldh, sH, mask, sweeps_out, st))) return err;
-  GemmArgs g = square_product(n, batch, t.V, np, m2, t.V, np, m2, e.Hw, np, m2, t.risk);
-  g.sym = 1;
-  if ((err = gemm_launch(g, PREC_F32, 1, 0, st))) return err;
-  if ((err = tri_check(t, e.Hw, mask, st))) return err;
   // a matrix whose vectors stay bad is flagged where the caller has no other solver for it
-  if ((err = tri_rescue(t, e.Hw, o.rescued ? nullptr : flags, mask, st))) return err;
-  g.active = t.bad;
-  if ((err = gemm_launch(g, PREC_F32, 1, 0, st))) return err;
-  GemmArgs u = square_product(n, batch, t.V, np, m2, e.Hw, np, m2, e.V2, np, m2, t.risk);
-  u.Cin = t.V; u.ldcin = np; u.sCin = m2;
-  u.alpha = -0.5f; u.beta = 1.5f;
-  if ((err = gemm_launch(u, PREC_F32, 0, 1, st))) return err;  // the Gram matrix is symmetric
+  int* const bad_flags = o.rescued ? nullptr : flags;
+  if (np <= kTriPolish) {
+    if ((err = tri_polish(t, e.Hw, e.V2, 0, mask, st))) return err;
+    if ((err = tri_rescue(t, e.Hw, bad_flags, mask, st))) return err;
+    if ((err = tri_polish(t, e.Hw, e.V2, 1, mask, st))) return err;
+  } else {
+    GemmArgs g = square_product(n, batch, t.V, np, m2, t.V, np, m2, e.Hw, np, m2, t.risk);
+    g.sym = 1;
+    if ((err = gemm_launch(g, PREC_F32, 1, 0, st))) return err;
+    if ((err = tri_check(t, e.Hw, mask, st))) return err;
+    if ((err = tri_rescue(t, e.Hw, bad_flags, mask, st))) return err;
+    g.active = t.bad;
+    if ((err = gemm_launch(g, PREC_F32, 1, 0, st))) return err;
+    GemmArgs u = square_product(n, batch, t.V, np, m2, e.Hw, np, m2, e.V2, np, m2, t.risk);
+    u.Cin = t.V; u.ldcin = np; u.sCin = m2;
+    u.alpha = -0.5f; u.beta = 1.5f;
+    if ((err = gemm_launch(u, PREC_F32, 0, 1, st))) return err;  // the Gram matrix is symmetric
+  }
   GemmArgs y = square_product(n, batch, H, ldh, sH, t.V, np, m2, e.Hw, np, m2, mask);  // H V
   y.B_alt = e.V2; y.b_sel = t.risk;
   if ((err = gemm_launch(y, PREC_F32, 0, 0, st))) return err;

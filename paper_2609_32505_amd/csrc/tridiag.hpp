@@ -8,6 +8,9 @@
 // registers, above it is matrix products.
 constexpr int kTriMax = 4096;
 constexpr int kTriSlab = 1024;
+// Up to kTriPolish every matrix gets the Newton-Schulz step, above it those with
+// close eigenvalues.
+constexpr int kTriPolish = 128;
 
 struct TriWs {
   int batch, n, np;  // np: leading dimension of every square array below
@@ -26,7 +29,7 @@ struct TriWs {
   float *S, *T4, *C;  // np > kTriSlab, batch x np x 128 each: Gram matrices and WY factors of 128
                      // reflectors, and 128 rows of products
   float* Y;          // np > kTriSlab, batch x np x np: T4^T V^T (may overlay Zb behind V)
-  int* risk;         // batch: 1 where eigenvalues nearly coincide
+  int* risk;         // batch: 1 where V gets the Newton-Schulz step: eigenvalues nearly coincide
   int* bad;          // batch: 1 where V was not orthonormal, 2 where it still is not
 };
 
@@ -37,6 +40,8 @@ struct TriWs {
 // other memory that is free by then, V may overlay Zb.
 // tri_check: bad[b] = 1 where max |G - I| > 1e-4 for the Gram matrix G of V,
 // among those of risk.
+// tri_polish: Gram matrix, tri_check and the Newton-Schulz step to V2, up to
+// kTriPolish.
 // tri_rescue: the vectors of close eigenvalues orthogonalised for the matrices of
 // bad, which is 2 (and flags[b] |= EIGH_NOT_CONVERGED, unless flags is null) where
 // they were too many.

@@ -931,12 +931,13 @@ __global__ __launch_bounds__(64 * W, TPW <= 2 ? 3 : 2) void k_tri_back(TriWs t, 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, kh = lane >> 5, ic = lane & 31;
   const int c = slab * 32 + ic;
   // eigenvalues closer than 1e-8 of the spectrum: their FP64 vectors may be
-  // short of orthogonal by more than FP32 rounding
+  // short of orthogonal by more than FP32 rounding.  Up to kTriPolish every matrix
+  // counts: its few reflections leave more than the Newton-Schulz step does
   if (slab == 0) {
     const double* lam = t.lam + (int64_t)b * ld;
     const double gap = 1e-8 * (lam[n - 1] - lam[0]);
-    for (int i = tid + 1; i < n; i += 64 * W)
-      if (!(lam[i] - lam[i - 1] > gap)) t.risk[b] = 1;
+    for (int i = tid; i < n; i += 64 * W)
+      if (n <= kTriPolish || (i > 0 && !(lam[i] - lam[i - 1] > gap))) t.risk[b] = 1;
   }
   const double* Z = t.Z + (int64_t)b * ld * ld;
   const float* HV = t.HV + (int64_t)b * ld * ld;
@@ -1060,7 +1061,94 @@ __global__ __launch_bounds__(256) void k_tri_dev(TriWs t, const float* G, const 
   if ((threadIdx.x & 63) == 0 && m > 1e-4f && isfinite(m)) t.bad[b] = 1;
 }
 
-// lam_k = v_k^T (H v_k), Y = H V, summed in FP64: a wave takes every blockDim /
+// The same two in one launch for matrices up to kTriPolish, with the Newton-Schulz
+// step V2 = V (3 I - G) / 2 of all of them: one workgroup per matrix, V and G in LDS
+// (pitch NP + 4), 16 x 16 x 4 products in the index order of k_cans_small.  The G of
+// a matrix of bad goes to Gm, for tri_rescue; again: those alone, after it.  Bound by
+// the loads of V and its barriers; as launches of their own, Gram matrix, test and
+// step took the EVD of 1 x 64^2 from 193 to 205 us and of 512 x 128^2 from 613 to 683.
+template <int NP>
+__global__ __launch_bounds__(8 * NP) void k_tri_polish(TriWs t, float* Gm, float* V2, int again, const int* mask) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  static_assert(NP == 64 || NP == 128, "two waves for 16 rows");
+  constexpr int LD = NP + 4, NT = 8 * NP, NW = NT / 64, T = NP / 16, TH = T / 2;
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  float *X = lds, *G = lds + NP * LD;
+  __shared__ float red[NW];
+  const int n = t.n, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, kq = lane >> 4;
+  for (int b = blockIdx.x; b < t.batch; b += gridDim.x) {
+    if ((mask && !mask[b]) || (again && !t.bad[b])) continue;
+    const int64_t o = (int64_t)b * t.np * t.np;
+    __syncthreads();  // the matrix before is done
+#pragma unroll
+    for (int q = 4 * tid; q < NP * NP; q += 4 * NT) {
+      const int i = q / NP, j = q - i * NP;
+      f4 v = *(const f4*)(t.V + o + (int64_t)min(i, n - 1) * t.np + j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = i < n && j + e < n ? v[e] : 0.f;
+      *(f4*)&X[i * LD + j] = v;
+    }
+    __syncthreads();
+    float m = 0.f;
+    for (int q = w; q < T * (T + 1) / 2; q += NW) {
+      int ti = 0, r = q;
+      while (r >= T - ti) { r -= T - ti; ++ti; }
+      const int tj = ti + r;
+      f4 acc = {0.f, 0.f, 0.f, 0.f};
+      const float* p = X + 4 * kq * LD + li;
+#pragma unroll
+      for (int k0 = 0; k0 < NP; k0 += 16, p += 16 * LD)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(p[u * LD + 16 * ti], p[u * LD + 16 * tj], acc, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = 16 * ti + 4 * kq + e, j = 16 * tj + li;
+        G[i * LD + j] = acc[e];
+        G[j * LD + i] = acc[e];
+        if (i < n && j < n) m = fmaxf(m, fabsf(acc[e] - (i == j ? 1.f : 0.f)));
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    if (lane == 0) red[w] = m;
+    __syncthreads();
+    for (int q = 0; q < NW; ++q) m = fmaxf(m, red[q]);
+    if (!again && m > 1e-4f && isfinite(m)) {
+      if (tid == 0) t.bad[b] = 1;
+      for (int q = tid; q < NP * NP; q += NT) {
+        const int i = q / NP, j = q - i * NP;
+        if (i < n && j < n) Gm[o + (int64_t)i * t.np + j] = G[i * LD + j];
+      }
+      continue;
+    }
+    // a wave: 16 rows, half of the columns
+    const int s = w >> 1, c0 = (w & 1) * TH;
+    f4 acc[TH];
+#pragma unroll
+    for (int c = 0; c < TH; ++c) acc[c] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int k0 = 0; k0 < NP; k0 += 16) {
+      const f4 av = *(const f4*)&X[(16 * s + li) * LD + k0 + 4 * kq];
+      f4 bv[TH];
+#pragma unroll
+      for (int c = 0; c < TH; ++c) bv[c] = *(const f4*)&G[(16 * (c0 + c) + li) * LD + k0 + 4 * kq];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int c = 0; c < TH; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[c][u], acc[c], 0, 0, 0);
+    }
+#pragma unroll
+    for (int c = 0; c < TH; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = 16 * s + 4 * kq + e, j = 16 * (c0 + c) + li;
+        if (i < n && j < n) V2[o + (int64_t)i * t.np + j] = 1.5f * X[i * LD + j] - 0.5f * acc[c][e];
+      }
+  }
+}
+
+// lam_k = v_k^T (H v_k) / v_k^T v_k, Y = H V, summed in FP64 (the norm of an FP32
+// vector is off by as much as the quotient otherwise): a wave takes every blockDim /
 // 64-th row of 64 columns.  Bound by reading V and Y once (256 x 512^2: 104 us,
 // where the full product V^T Y took 500; 4096^2: 42 for 772, and its FP32 sums of
 // one sign were the largest error of the eigenvalues there).
@@ -1068,19 +1156,27 @@ __global__ __launch_bounds__(1024) void k_tri_rayleigh(TriWs t, const float* V2,
                                                        const int* mask) {
   const int b = blockIdx.y;
   if (mask && !mask[b]) return;
-  __shared__ double part[16][64];
+  __shared__ double part[2][16][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int c = blockIdx.x * 64 + lane;  // c < np: a multiple of 64
   const int64_t o = (int64_t)b * t.np * t.np + c;
   const float* v = (t.risk[b] ? V2 : t.V) + o;
-  double s = 0.0;
+  double s = 0.0, vv = 0.0;
 #pragma unroll 8
-  for (int r = w; r < t.n; r += nw) s = fma((double)v[(int64_t)r * t.np], (double)Y[o + (int64_t)r * t.np], s);
-  part[w][lane] = s;
+  for (int r = w; r < t.n; r += nw) {
+    const double x = (double)v[(int64_t)r * t.np];
+    s = fma(x, (double)Y[o + (int64_t)r * t.np], s);
+    vv = fma(x, x, vv);
+  }
+  part[0][w][lane] = s;
+  part[1][w][lane] = vv;
   __syncthreads();
   if (w == 0 && c < t.n) {
-    for (int q = 1; q < nw; ++q) s += part[q][lane];
-    lam[(int64_t)b * t.n + c] = (float)s;
+    for (int q = 1; q < nw; ++q) {
+      s += part[0][q][lane];
+      vv += part[1][q][lane];
+    }
+    lam[(int64_t)b * t.n + c] = (float)(vv > 0.0 ? s / vv : s);
   }
 }
 
@@ -1426,5 +1522,14 @@ static hipError_t tri_rayleigh(const TriWs& t, const float* V2, const float* Y, 
 
 static hipError_t tri_rescue(const TriWs& t, const float* G, int* flags, const int* mask, hipStream_t st) {
   hipLaunchKernelGGL(k_tri_rescue, dim3(t.batch), dim3(1024), (size_t)t.n * 16, st, t, G, flags, mask);
+  return hipGetLastError();
+}
+
+static hipError_t tri_polish(const TriWs& t, float* G, float* V2, int again, const int* mask, hipStream_t st) {
+  const size_t lds = (size_t)2 * t.np * (t.np + 4) * sizeof(float);
+  const dim3 grid(again ? std::min(t.batch, 64) : t.batch);
+  if (t.np == 64) hipLaunchKernelGGL(k_tri_polish<64>, grid, dim3(512), lds, st, t, G, V2, again, mask);
+  else if (t.np == 128) hipLaunchKernelGGL(k_tri_polish<128>, grid, dim3(1024), lds, st, t, G, V2, again, mask);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }

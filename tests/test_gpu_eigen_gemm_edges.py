@@ -148,6 +148,27 @@ def test_too_many_coinciding_eigenvalues_are_flagged(api):
     assert list(api.info_to_numpy(info)["flags"] & FAILED) == [32, 0]
 
 
+# Small matrices to an EPS or two: a Rayleigh quotient over v^T v has the error of the
+# vector squared, which leaves the rounding of H v and of the result; a Newton-Schulz
+# step leaves V orthonormal to its own rounding (2 EPS a column's norm, EPS sqrt(2) an
+# angle, and the rounding of the step's sums again).
+@pytest.mark.parametrize("b,n", [(256, 5), (256, 16), (128, 33), (64, 64), (64, 65), (32, 100), (32, 128)])
+def test_eigh_small_accuracy(api, b, n):
+    import torch
+    print(f"small accuracy {b} x {n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    Q = torch.linalg.qr(torch.randn(b, n, n, generator=g, device="cuda", dtype=torch.float64))[0]
+    lo = torch.arange(n, 0, -1, device="cuda", dtype=torch.float64) / n
+    H = ((Q * lo) @ Q.transpose(1, 2).contiguous()).float()
+    lam, V, info = api.eigh(H)
+    assert (api.info_to_numpy(info)["flags"] & FAILED == 0).all()
+    ref = torch.linalg.eigvalsh(H.double().cpu()).flip(-1).cuda()
+    V = V.double()
+    assert float(torch.linalg.norm(lam.double() - ref) / torch.linalg.norm(ref)) <= 2 * EPS
+    G = V.transpose(1, 2).contiguous() @ V - torch.eye(n, dtype=torch.float64, device="cuda")
+    assert float(torch.linalg.norm(G) / np.sqrt(b * n)) <= 4 * EPS
+
+
 def test_eigh_nan_is_flagged_alone(api):
     import torch
     H = torch.randn(3, 70, 70, generator=torch.Generator().manual_seed(5))
