@@ -1056,6 +1056,15 @@ svdp_status svd_core(Ctx& c, float* U, int64_t ldu, int64_t sU, float* S, int64_
 
 // ---------------------------------------------------------------- spectral divide and conquer
 
+// Products of the divide and conquer: the eigenvalues come from the diagonal of
+// T = Q^T M Q, sums of one sign, and their error at 4096^2 is 1.2e-7 with exact
+// sums, 8.0e-7 without (21.2 ms at 2048^2 and 96.4 at 4096^2 either way).
+GemmArgs dc_gemm(int M, int N, int K, int batch) {
+  GemmArgs g = gemm_base(M, N, K, batch);
+  g.exact_sums = 1;
+  return g;
+}
+
 // The polar step of the split: one n x n matrix, conservative FP32 CANS with
 // the caller's CANS settings.
 svdp_params dc_polar_params(const svdp_params* p) {
@@ -1206,7 +1215,7 @@ svdp_status dc_split(svdp_handle* h, const svdp_params* p, const DcWs& w, DcPiec
   HIPCHK(dc_signs_launch(w.cs, s, w.k, st), "dc signs");
   // Y = (X + W X diag(cs)) / 2, cs = +1 for the first k columns
   auto range = [&](const float* X, float* Y) {
-    GemmArgs g = gemm_base(s, s, s, 1);
+    GemmArgs g = dc_gemm(s, s, s, 1);
     g.A = c.w.X0; g.A_alt = c.w.X1; g.a_sel = c.w.where; g.lda = s; g.sA = ss;
     g.B = X; g.ldb = s; g.sB = ss;
     g.C = Y; g.ldc = s; g.sC = ss;
@@ -1219,13 +1228,13 @@ svdp_status dc_split(svdp_handle* h, const svdp_params* p, const DcWs& w, DcPiec
   // Y2 <- Y2 - Q1 (Q1^T Y2) for the s x (s - k) block at Y (pitch s), Q1 the
   // first k columns of pc.Q
   auto project = [&](float* Y2) -> hipError_t {
-    GemmArgs g = gemm_base(k, s - k, s, 1);
+    GemmArgs g = dc_gemm(k, s - k, s, 1);
     g.A = pc.Q; g.lda = s; g.sA = ss;
     g.B = Y2; g.ldb = s; g.sB = ss;
     g.C = w.A; g.ldc = s - k; g.sC = ss;
     hipError_t e = gemm_launch(g, PREC_F32, 1, 0, st);
     if (e) return e;
-    GemmArgs u = gemm_base(s, s - k, k, 1);
+    GemmArgs u = dc_gemm(s, s - k, k, 1);
     u.A = pc.Q; u.lda = s; u.sA = ss;
     u.B = w.A; u.ldb = s - k; u.sB = ss;
     u.C = Y2; u.ldc = s; u.sC = ss;
@@ -1258,7 +1267,7 @@ svdp_status dc_split(svdp_handle* h, const svdp_params* p, const DcWs& w, DcPiec
     float* src = w.Om + c0;
     float* dst = pc.Q + c0;
     for (int it = 0; it < 3; ++it) {
-      GemmArgs g = gemm_base(cols, cols, s, 1);  // G = Y^T Y
+      GemmArgs g = dc_gemm(cols, cols, s, 1);  // G = Y^T Y
       g.A = src; g.lda = s; g.sA = ss;
       g.B = src; g.ldb = s; g.sB = ss;
       g.C = w.A; g.ldc = cols; g.sC = ss;
@@ -1266,7 +1275,7 @@ svdp_status dc_split(svdp_handle* h, const svdp_params* p, const DcWs& w, DcPiec
       hipError_t e = gemm_launch(g, PREC_F32, 1, 0, st);
       if (e) return e;
       if (it == 2 && (e = dc_dev_launch(w.A, cols, w.part, dev, st))) return e;
-      GemmArgs u = gemm_base(s, cols, cols, 1);  // Z = 1.5 Y - 0.5 Y G
+      GemmArgs u = dc_gemm(s, cols, cols, 1);  // Z = 1.5 Y - 0.5 Y G
       u.A = src; u.lda = s; u.sA = ss;
       u.B = w.A; u.ldb = cols; u.sB = ss;
       u.C = dst; u.ldc = s; u.sC = ss;
@@ -1281,12 +1290,12 @@ svdp_status dc_split(svdp_handle* h, const svdp_params* p, const DcWs& w, DcPiec
   for (int pass = 0; pass < 2; ++pass) HIPCHK(project(w.Om + k), "dc project 2");
   HIPCHK(newton_schulz(k, s - k, w.cpl + 4), "dc orth Q2");
   // T = Q^T (M Q) and its coupling block
-  GemmArgs g1 = gemm_base(s, s, s, 1);
+  GemmArgs g1 = dc_gemm(s, s, s, 1);
   g1.A = pc.M; g1.lda = pc.ldm; g1.sA = ss;
   g1.B = pc.Q; g1.ldb = s; g1.sB = ss;
   g1.C = w.Om; g1.ldc = s; g1.sC = ss;
   HIPCHK(gemm_launch(g1, PREC_F32, 0, 0, st), "dc M Q");
-  GemmArgs g2 = gemm_base(s, s, s, 1);
+  GemmArgs g2 = dc_gemm(s, s, s, 1);
   g2.A = pc.Q; g2.lda = s; g2.sA = ss;
   g2.B = w.Om; g2.ldb = s; g2.sB = ss;
   g2.C = pc.T; g2.ldc = s; g2.sC = ss;
@@ -1402,12 +1411,12 @@ svdp_status eigh_dc_one(svdp_handle* h, const svdp_params* p, const DcWs& w, con
     if (!pc.split) continue;
     const int k = pc.k, s = pc.s;
     const int64_t ss = (int64_t)s * s, d = (int64_t)k * s + k;
-    GemmArgs v1 = gemm_base(s, k, k, 1);
+    GemmArgs v1 = dc_gemm(s, k, k, 1);
     v1.A = pc.Q; v1.lda = s; v1.sA = ss;
     v1.B = pc.W; v1.ldb = s; v1.sB = ss;
     v1.C = pc.V; v1.ldc = pc.ldv; v1.sC = ss;
     HIPCHK(gemm_launch(v1, PREC_F32, 0, 0, st), "dc V1");
-    GemmArgs v2 = gemm_base(s, s - k, s - k, 1);
+    GemmArgs v2 = dc_gemm(s, s - k, s - k, 1);
     v2.A = pc.Q + k; v2.lda = s; v2.sA = ss;
     v2.B = pc.W + d; v2.ldb = s; v2.sB = ss;
     v2.C = pc.V + k; v2.ldc = pc.ldv; v2.sC = ss;

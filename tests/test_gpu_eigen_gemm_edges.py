@@ -333,3 +333,19 @@ def test_tall_infinity_is_flagged_alone(api):
         assert torch.equal(S[0], ref[0])
         for x, y in zip((U, S, V), out[0]):
             assert torch.equal(x.isnan(), y.isnan()) and torch.equal(x.nan_to_num(), y.nan_to_num())
+
+
+# Eigenvalues of the divide and conquer are sums over n indices of one sign; the
+# running sum's rounding grows with its length.  A few EPS of the largest: the rounding
+# of the result, of the shift and of eight partial sums.
+@pytest.mark.parametrize("n", [1000, 2048, 4096])
+def test_dc_eigenvalues(api, n):
+    import torch
+    print(f"dc eigenvalues {n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    Q = torch.linalg.qr(torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64))[0]
+    lam = torch.linspace(1.0, 0.01, n, device="cuda", dtype=torch.float64)
+    H = ((Q * lam) @ Q.T).float()
+    out, V, info = api.eigh_dc(H[None])
+    assert (api.info_to_numpy(info)["flags"] & FAILED == 0).all()
+    assert float((out[0].double() - lam).abs().max()) <= 5 * EPS
