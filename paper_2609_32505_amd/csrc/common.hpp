@@ -49,6 +49,7 @@ struct GemmArgs {
   void* C_bf;          // (same leading dimension and stride as C), else to C
   float* conv;         // per matrix and wave sub-tile (gemm_conv_slots slots): sum (out - Cin)^2, sum out^2
   int sym;             // output symmetric: upper tiles computed, mirrored
+  int exact_small;     // FP32: tiles of operands below 2^-108 keep all bits (plain sums, slow)
   int exact_sums;      // FP32: running sums are flushed every 512 indices (LONG of k_gemm_x3)
   int out_bf16, in_bf16, cin_bf16;
   void* Ct; int64_t ldct, sCt;  // out_bf16: also write the output transposed, Ct[j, i] (BF16)

@@ -202,6 +202,23 @@ def test_split_product_edges(api, b, n):
     assert ((dH.cpu().double() - ref).abs() <= (np.sqrt(n) + 8) * EPS * mag).all()
 
 
+# the low terms of small operands underflow in 16 bits; FP32 holds them to 2^-126
+@pytest.mark.parametrize("e", [-100, -107, -109, -114, -118])
+@pytest.mark.parametrize("b,n", [(2, 5), (2, 64), (1, 130), (48, 384)])
+def test_split_product_small_operands(api, b, n, e):
+    import torch
+    print(f"small operands b={b} n={n} 2^{e}", flush=True)
+    g = torch.Generator().manual_seed(n)
+    V = torch.randn(b, n, n, generator=g)
+    d = torch.randn(b, n, generator=g) * 2.0 ** e
+    lam = torch.arange(n, 0, -1).float().expand(b, n).contiguous()
+    dH = api.eigh_bwd(lam.cuda(), V.cuda(), dlam=d.cuda())
+    V, d = V.double(), d.double()
+    ref = (V * d[:, None]) @ V.transpose(1, 2)
+    mag = (V * d[:, None]).abs() @ V.abs().transpose(1, 2)
+    assert bool(((dH.cpu().double() - ref).abs() <= (np.sqrt(n) + 8) * EPS * mag + n * 2.0 ** -148).all())
+
+
 def test_split_product_keeps_infinities(api):
     import torch
     n = 40
