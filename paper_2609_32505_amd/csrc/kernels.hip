@@ -1535,7 +1535,10 @@ bool cans_small_fits(int64_t m, int64_t n) {
 template <int NP, typename F>
 static hipError_t cans_small_np_launch(const CansSmall& a, hipStream_t st) {
   const size_t lds = cans_small_lds(a.m, a.n, sizeof(F));
-  hipError_t e = hipFuncSetAttribute((const void*)k_cans_small<NP, F>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  // the same value in every call: the limit is the function's, not the launch's, and
+  // another thread may launch with less at the same time
+  hipError_t e = hipFuncSetAttribute((const void*)k_cans_small<NP, F>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)kCansSmallLds);
   if (e) return e;
   // a wave for each strip of 16 rows
   const int nw = std::min(16, std::max(4, cdiv(a.m, 16)));

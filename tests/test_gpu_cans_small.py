@@ -110,3 +110,32 @@ def test_polar_stop_test(api, n, poly):
     assert alone["iters"][0] == info["iters"][2]
     short = api.info_to_numpy(api.polar_fwd(d[:1], cache=False, poly=poly, max_iters=3, pre_iters=2)[-1])
     assert short["iters"][0] == 3 and short["flags"][0] & 1
+
+
+# One workgroup's LDS limit is a property of the kernel: threads that launch it with
+# different sizes at the same time, each on its own stream and handle
+def test_small_sizes_from_two_threads():
+    import threading
+    import torch
+    from paper_2609_32505_amd import api
+    g = torch.Generator(device="cuda").manual_seed(3)
+    A = [torch.randn(2, m, n, generator=g, device="cuda") for m, n in ((176, 128), (100, 100))]
+    ref = [api.svd_fwd(a)[1] for a in A]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(i):
+        h, st = api.Handle(), torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            for _ in range(20):
+                S = api.svd_fwd(A[i], handle=h)[1]
+                st.synchronize()
+                if not torch.equal(S, ref[i]):
+                    bad.append(i)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
