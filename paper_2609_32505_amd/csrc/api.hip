@@ -445,10 +445,11 @@ GemmArgs gemm_base(int M, int N, int K, int batch) {
   return g;
 }
 
-// Products of the backward passes: gradients of any size keep the bits of FP32.  Not
-// so the forward passes', whose eigenvectors of T decay below 2^-108 in whole tiles
-// (1 x 4096^2 would take 111 ms for 84); H of an input below 2^-110 loses low bits.
-GemmArgs bwd_gemm(int M, int N, int K, int batch) {
+// Products of the caller's own values, of any size: the backward passes' and H = W^T A
+// keep the bits of FP32 (H of an input of 2^-114: 2.3e-7 off, 4.3e-7 without).  Not so
+// the forward passes' others, whose eigenvectors of T decay below 2^-108 in whole
+// tiles (1 x 4096^2 would take 111 ms for 84).
+GemmArgs any_size_gemm(int M, int N, int K, int batch) {
   GemmArgs g = gemm_base(M, N, K, batch);
   g.exact_small = 1;
   return g;
@@ -823,7 +824,7 @@ svdp_status final_residual(Ctx& c, const int* mask) {
 svdp_status form_h(Ctx& c, const int* mask) {
   FwdWs& w = c.w;
   const int B = c.batch, m = c.m, n = c.n;
-  GemmArgs g = gemm_base(n, n, m, B);
+  GemmArgs g = any_size_gemm(n, n, m, B);
   g.A = w.X0; g.A_alt = w.X1; g.a_sel = w.where; g.lda = n; g.sA = (int64_t)m * n;
   g.B = c.A; g.ldb = c.lda; g.sB = c.sA;
   g.C = w.G; g.ldc = n; g.sC = (int64_t)n * n;
@@ -1813,7 +1814,7 @@ svdp_status svdp_eigh_bwd(svdp_handle* h, const svdp_params* p, const float* lam
   float* C = c.take<float>((size_t)B * n * n);
   float* T = c.take<float>((size_t)B * n * n);
   if (dV) {  // P = V^T dV
-    GemmArgs g = bwd_gemm(n, n, n, B);
+    GemmArgs g = any_size_gemm(n, n, n, B);
     g.A = V; g.lda = ldv; g.sA = sV;
     g.B = dV; g.ldb = lddv; g.sB = sdV;
     g.C = P; g.ldc = n; g.sC = (int64_t)n * n;
@@ -1822,14 +1823,14 @@ svdp_status svdp_eigh_bwd(svdp_handle* h, const svdp_params* p, const float* lam
   HIPCHK(sylvester_launch(2, nullptr, dV ? P : nullptr, lam, slam, dlam, sdlam, nullptr, B, n, q.eps_K, 0.0, C, st),
          "eigh bwd scaling");
   {  // T = V C
-    GemmArgs g = bwd_gemm(n, n, n, B);
+    GemmArgs g = any_size_gemm(n, n, n, B);
     g.A = V; g.lda = ldv; g.sA = sV;
     g.B = C; g.ldb = n; g.sB = (int64_t)n * n;
     g.C = T; g.ldc = n; g.sC = (int64_t)n * n;
     HIPCHK(gemm_launch(g, PREC_F32, 0, 0, st), "V C");
   }
   {  // dH = T V^T
-    GemmArgs g = bwd_gemm(n, n, n, B);
+    GemmArgs g = any_size_gemm(n, n, n, B);
     g.A = T; g.lda = n; g.sA = (int64_t)n * n;
     g.B = V; g.ldb = ldv; g.sB = sV;
     g.C = dH; g.ldc = lddh; g.sC = sdH;
@@ -1857,14 +1858,14 @@ svdp_status svd_bwd_impl(const svdp_params* p, const float* U, int64_t ldu, int6
   float* Z = c.take<float>((size_t)B * m * n);
   float* D = c.take<float>((size_t)B * n);
   if (dU) {  // Ahat = U^T dU
-    GemmArgs g = bwd_gemm(n, n, m, B);
+    GemmArgs g = any_size_gemm(n, n, m, B);
     g.A = U; g.lda = ldu; g.sA = sU;
     g.B = dU; g.ldb = lddu; g.sB = sdU;
     g.C = X1; g.ldc = n; g.sC = (int64_t)n * n;
     HIPCHK(gemm_launch(g, PREC_F32, 1, 0, st), "U^T dU");
   }
   if (dV) {  // P = V^T dV
-    GemmArgs g = bwd_gemm(n, n, n, B);
+    GemmArgs g = any_size_gemm(n, n, n, B);
     g.A = V; g.lda = ldv; g.sA = sV;
     g.B = dV; g.ldb = lddv; g.sB = sdV;
     g.C = X2; g.ldc = n; g.sC = (int64_t)n * n;
@@ -1874,7 +1875,7 @@ svdp_status svd_bwd_impl(const svdp_params* p, const float* U, int64_t ldu, int6
   HIPCHK(sylvester_launch(0, dU ? X1 : nullptr, dV ? X2 : nullptr, S, sS, dS, sdS, D, B, n, p->eps_K, p->eps_T, Y,
                           st), "sylvester");
   {  // Z = 2 U (S Y) + dU diag(D)
-    GemmArgs g = bwd_gemm(m, n, n, B);
+    GemmArgs g = any_size_gemm(m, n, n, B);
     g.A = U; g.lda = ldu; g.sA = sU;
     g.B = Y; g.ldb = n; g.sB = (int64_t)n * n;
     g.C = Z; g.ldc = n; g.sC = (int64_t)m * n;
@@ -1886,7 +1887,7 @@ svdp_status svd_bwd_impl(const svdp_params* p, const float* U, int64_t ldu, int6
     HIPCHK(gemm_launch(g, PREC_F32, 0, 0, st), "Z");
   }
   {  // dA = Z V^T
-    GemmArgs g = bwd_gemm(m, n, n, B);
+    GemmArgs g = any_size_gemm(m, n, n, B);
     g.A = Z; g.lda = n; g.sA = (int64_t)m * n;
     g.B = V; g.ldb = ldv; g.sB = sV;
     g.C = dA; g.ldc = ldda; g.sC = sdA;
@@ -1998,31 +1999,31 @@ svdp_status polar_bwd(svdp_handle* h, const svdp_params* p, const float* A, int6
     Sx = Sown; Vx = Vown; sSx = n; ldvx = n; sVx = (int64_t)n * n;
   }
   {  // MV = A V
-    GemmArgs g = bwd_gemm(m, n, n, B);
+    GemmArgs g = any_size_gemm(m, n, n, B);
     g.A = A; g.lda = lda; g.sA = sA;
     g.B = Vx; g.ldb = ldvx; g.sB = sVx;
     g.C = MV; g.ldc = n; g.sC = (int64_t)m * n;
     HIPCHK(gemm_launch(g, PREC_F32, 0, 0, st), "A V");
   }
   if (dW) {
-    GemmArgs g = bwd_gemm(m, n, n, B);  // dW V
+    GemmArgs g = any_size_gemm(m, n, n, B);  // dW V
     g.A = dW; g.lda = lddw; g.sA = sdW;
     g.B = Vx; g.ldb = ldvx; g.sB = sVx;
     g.C = WV; g.ldc = n; g.sC = (int64_t)m * n;
     HIPCHK(gemm_launch(g, PREC_F32, 0, 0, st), "dW V");
-    GemmArgs q = bwd_gemm(n, n, m, B);  // (A V)^T (dW V)
+    GemmArgs q = any_size_gemm(n, n, m, B);  // (A V)^T (dW V)
     q.A = MV; q.lda = n; q.sA = (int64_t)m * n;
     q.B = WV; q.ldb = n; q.sB = (int64_t)m * n;
     q.C = X2; q.ldc = n; q.sC = (int64_t)n * n;
     HIPCHK(gemm_launch(q, PREC_F32, 1, 0, st), "(AV)^T dW V");
   }
   if (dH) {
-    GemmArgs g = bwd_gemm(n, n, n, B);  // V^T dH
+    GemmArgs g = any_size_gemm(n, n, n, B);  // V^T dH
     g.A = Vx; g.lda = ldvx; g.sA = sVx;
     g.B = dH; g.ldb = lddh; g.sB = sdH;
     g.C = T1; g.ldc = n; g.sC = (int64_t)n * n;
     HIPCHK(gemm_launch(g, PREC_F32, 1, 0, st), "V^T dH");
-    GemmArgs q = bwd_gemm(n, n, n, B);  // (V^T dH) V
+    GemmArgs q = any_size_gemm(n, n, n, B);  // (V^T dH) V
     q.A = T1; q.lda = n; q.sA = (int64_t)n * n;
     q.B = Vx; q.ldb = ldvx; q.sB = sVx;
     q.C = X1; q.ldc = n; q.sC = (int64_t)n * n;
@@ -2032,7 +2033,7 @@ svdp_status polar_bwd(svdp_handle* h, const svdp_params* p, const float* A, int6
   HIPCHK(sylvester_launch(1, dH ? X1 : nullptr, dW ? X2 : nullptr, Sx, sSx, nullptr, 0, D, B, n, p->eps_K,
                           p->eps_T, Y, st), "sylvester");
   {  // Z = 2 (A V) Xt + (dW V) diag(D)
-    GemmArgs g = bwd_gemm(m, n, n, B);
+    GemmArgs g = any_size_gemm(m, n, n, B);
     g.A = MV; g.lda = n; g.sA = (int64_t)m * n;
     g.B = Y; g.ldb = n; g.sB = (int64_t)n * n;
     g.C = Z; g.ldc = n; g.sC = (int64_t)m * n;
@@ -2044,7 +2045,7 @@ svdp_status polar_bwd(svdp_handle* h, const svdp_params* p, const float* A, int6
     HIPCHK(gemm_launch(g, PREC_F32, 0, 0, st), "Z");
   }
   {  // dA = Z V^T
-    GemmArgs g = bwd_gemm(m, n, n, B);
+    GemmArgs g = any_size_gemm(m, n, n, B);
     g.A = Z; g.lda = n; g.sA = (int64_t)m * n;
     g.B = Vx; g.ldb = ldvx; g.sB = sVx;
     g.C = dA; g.ldc = ldda; g.sC = sdA;

@@ -219,6 +219,22 @@ def test_split_product_small_operands(api, b, n, e):
     assert bool(((dH.cpu().double() - ref).abs() <= (np.sqrt(n) + 8) * EPS * mag + n * 2.0 ** -148).all())
 
 
+# the same for H = sym(W^T A) of small inputs
+@pytest.mark.parametrize("e", [-100, -109, -114, -118])
+@pytest.mark.parametrize("b,m,n", [(2, 9, 5), (4, 74, 64), (2, 210, 200), (16, 400, 390)])
+def test_polar_h_of_small_inputs(api, b, m, n, e):
+    import torch
+    print(f"small inputs {b} x {m} x {n} 2^{e}", flush=True)
+    g = torch.Generator().manual_seed(n)
+    A = torch.randn(b, m, n, generator=g) * 2.0 ** e
+    W, H, *_, info = api.polar_fwd(A.cuda(), cache=False)
+    assert (api.info_to_numpy(info)["flags"] & FAILED == 0).all()
+    W, H, A = W.cpu().double(), H.cpu().double(), A.double()
+    ref, mag = W.transpose(1, 2) @ A, W.abs().transpose(1, 2) @ A.abs()
+    ref, mag = 0.5 * (ref + ref.transpose(1, 2)), 0.5 * (mag + mag.transpose(1, 2))
+    assert bool(((H - ref).abs() <= (np.sqrt(m) + 8) * EPS * mag + m * 2.0 ** -148).all())
+
+
 def test_split_product_keeps_infinities(api):
     import torch
     n = 40
