@@ -27,7 +27,7 @@
  *     the bounded paths' fallback test (learned / user bounds), the QR step
  *     of Algorithm 1 when it runs blocked (n > 512), and the EVD step of a
  *     single FP32 matrix from n = 2048: one read of whether its eigenvectors
- *     are orthonormal, and where they are not, and above n = 4096, the divide
+ *     could be made orthonormal, and where not, and above n = 4096, the divide
  *     and conquer of svdp_eigh_dc (two reads per split); svdp_host_syncs()
  *     counts them.  That second solver also enlarges svd_polar_fwd's workspace by the
  *     divide and conquer's (SVDP_OP_EIGH_DC's for batch 1).
@@ -91,7 +91,9 @@ typedef enum {
 #define SVDP_FLAG_RANK_DEFICIENT 8       /* some | |U_i| - 1 | > eps_qr; U was orthogonalised by QR
                                             (Algorithm 1), zero columns completed */
 #define SVDP_FLAG_NONFINITE 16           /* non-finite input or result */
-#define SVDP_FLAG_EIGH_NOT_CONVERGED 32  /* Jacobi hit max_sweeps, or V is not orthonormal */
+#define SVDP_FLAG_EIGH_NOT_CONVERGED 32  /* Jacobi hit max_sweeps; above n = 1024 also: more
+                                            eigenvalues coincide than a few seconds of
+                                            orthogonalisation settle, V is not orthonormal */
 
 typedef struct {
   int64_t batch, m, n;     /* m >= n >= 1 */
@@ -125,7 +127,7 @@ typedef struct {
                               reaches this value, BF16 steps after it (0.2).  BF16 rounding
                               while a singular value is still small rotates its singular
                               vectors and moves the small singular values; the BF16
-                              correction (bf16_correct) removes that to first order.  With
+                              correction (bf16_correct) removes that to second order.  With
                               it, on 256 x 512^2 with sigma in [1e-3, 1], the largest
                               per-value relative sigma error against the FP32 path is 1e-4
                               from 0.5 down to 0.2 and 2e-4 at 0.1; at 0.01 it is 2e-2.

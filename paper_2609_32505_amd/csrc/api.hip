@@ -995,10 +995,11 @@ svdp_status svd_tail(Ctx& c, float* U, int64_t ldu, int64_t sU, float* S, int64_
   const float* Vb = V;
   int64_t ldvb = ldv, svb = sV;
   if (p->bf16_correct && p->precision == SVDP_PREC_BF16 && !mask) {
-    // First-order correction of the BF16-rounded polar factor (the bounded
-    // path's first pass; its fallback reruns are FP32).  P = V^T (W^T A) V is
-    // the eigensolver's last restart measure T (in Vw, working order, read
-    // through perm); polar_fix gives S~/2 and the corrected singular values;
+    // Correction of the BF16-rounded polar factor (the bounded path's first
+    // pass; its fallback reruns are FP32).  P = V^T (W^T A) V is the
+    // eigensolver's T (V^T H V of the tridiagonal route, the Jacobi's last
+    // restart measure; in Vw, working order, read through perm); polar_fix gives
+    // S~/2 and the corrected singular values;
     // U = W V exp(-S~/2) and V <- V exp(S~/2), to second order.  Scratch: the
     // eigensolver's working copies (np >= n), free once it returned.
     const int64_t n2 = (int64_t)n * n, np2 = (int64_t)e.np * e.np;

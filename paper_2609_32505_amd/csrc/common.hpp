@@ -10,13 +10,6 @@ typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 
 #define SVDP_DEV __device__ __forceinline__
 
-// One batched GEMM launch: out[b] = epilogue(op(A[b]) * op(B[b])).
-// Row-major storage.  op(A) is M x K: A[i*lda + k] (ta = 0) or A[k*lda + i]
-// (ta = 1).  op(B) is K x N: B[k*ldb + j] (tb = 0) or B[j*ldb + k] (tb = 1).
-// Epilogue (per matrix b, entry (i, j)):
-//   out = s_acc * acc * cs[j] + s_in * Cin[i, j] * csin[j]
-// where (s_in, s_acc) = coef[b*coef_bstride + coef_idx] when coef is set,
-// else (beta, alpha); cs / csin default to 1 when null.
 // The stop test of the CANS step before (conv: the change and output sums of
 // squares of its update, `slots` pairs per matrix; nullptr: none).
 struct StopTest {
@@ -27,6 +20,13 @@ struct StopTest {
   const int* iter_base; int base_stride;  // iters[b] = iter_base[b * base_stride] + k + 1 (base 0 when null)
 };
 
+// One batched GEMM launch: out[b] = epilogue(op(A[b]) * op(B[b])).
+// Row-major storage.  op(A) is M x K: A[i*lda + k] (ta = 0) or A[k*lda + i]
+// (ta = 1).  op(B) is K x N: B[k*ldb + j] (tb = 0) or B[j*ldb + k] (tb = 1).
+// Epilogue (per matrix b, entry (i, j)):
+//   out = s_acc * acc * cs[j] + s_in * Cin[i, j] * csin[j]
+// where (s_in, s_acc) = coef[b*coef_bstride + coef_idx] when coef is set,
+// else (beta, alpha); cs / csin default to 1 when null.
 struct GemmArgs {
   int M, N, K, batch;
   const void* A; int64_t lda, sA;

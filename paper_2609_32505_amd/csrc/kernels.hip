@@ -206,8 +206,9 @@ SVDP_DEV double wave_sum(double v) {
 // steps that a schedule runs in BF16 round X and G to BF16 where the GEMM path
 // stores them so.  F: FP32, or FP64 where a step is all latency and one small
 // singular value's error is not averaged out over many (cans_small_launch).
-// Bound by FP32 MFMA and by the latency of two barriers a step: one step of one
-// 64 x 64 matrix takes about 3 us, where the product, update and stop test as
+// Bound by the latency of two barriers a step and, of many matrices, by no one
+// unit (1024 x 32^2: MFMA busy 22%, VALU 26%, LDS 34%): one step of one 64 x 64
+// matrix takes about 3 us, where the product, update and stop test as
 // launches of their own took 14, and 7 more for each step of the enqueued
 // budget after the last.  A wave owns strips of 16 rows of X in the update (so
 // it may overwrite them at once) and tiles of G's upper triangle in the product;
@@ -819,7 +820,7 @@ __global__ void k_copy(const float* src, int64_t lds, int64_t ss, const int* sel
 
 // ------------------------------------------------------------ polar factor correction
 
-// First-order correction of a polar factor W = W_t (I + S) (S skew, small:
+// Correction of a polar factor W = W_t (I + S), to second order in S (skew, small:
 // the rounding of a BF16 iterate) from P = V^T (W^T A) V, with (lam, V) the
 // eigenpairs of sym(W^T A) (lam_i = sgn_i s_i).  P is the eigensolver's last
 // T = V_w^T (W^T A) V_w (working column order) in sorted order:

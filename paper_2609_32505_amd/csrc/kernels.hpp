@@ -54,7 +54,7 @@ hipError_t cans_check_launch(const StopTest& s, int batch, hipStream_t st);
 // Most slots at which the next product takes the stop test: adding 512 pairs
 // costs each of its workgroups about 1 us, a launch of its own 6 to 10 us a step
 // (24 x 333 x 257 step: 2545 -> 2137 us, 64 x 256^2: 2771 -> 2490).  One 4096^2
-// matrix has 16384, which every workgroup of its product would read; one launch
+// matrix has 4096, which every workgroup of its product would read; one launch
 // of one workgroup adds them in 4 us.
 constexpr int kStopSlots = 512;
 // residual[b] = |G - I|_F / sqrt(n) from a Gram matrix G (FP32 or BF16);
@@ -97,7 +97,7 @@ hipError_t sylvester_launch(int mode, const float* X1, const float* X2, const fl
 // out = (in + in^T) / 2 into a strided destination
 hipError_t symmetrize_launch(const float* in, int batch, int n, float* out, int64_t ldo,
                              int64_t so, hipStream_t st);
-// First-order correction of a BF16-rounded polar factor from
+// Correction of a BF16-rounded polar factor, to second order, from
 // P = V^T (W^T A) V, gathered as T[perm_i, perm_j] from the eigensolver's
 // last T (working order, leading dimension ldt, batch stride sT), and the
 // eigenpairs (lam, V) of sym(W^T A): lam = sgn * S (S magnitudes, snew a

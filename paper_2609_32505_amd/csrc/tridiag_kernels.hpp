@@ -348,7 +348,8 @@ __global__ __launch_bounds__(NT) void k_tri_reduce(TriWs t, int cols, const int*
 // updates.  p (by parity of j) and the scale are kept in T, which is free here.
 // Latency and the launch bound it for few matrices (5.5 us a column of one
 // 1024^2 matrix, where k_tri_reduce takes 23), the stream of A for more and for
-// large ones (11.6 us on average at 4096^2: 43 MB read and written, 7.4 TB/s).
+// large ones (11.5 us on average at 4096^2: 50 MB read and written beyond the L2,
+// 4.4 TB/s, where a large copy reaches 4.7).
 template <int NT, int NCH>
 __global__ __launch_bounds__(NT) void k_tri_column(TriWs t, int j, int js, int G, const int* mask) {
   constexpr int NW = NT / 64, U = 16 / NCH;
@@ -705,10 +706,11 @@ SVDP_DEV double pivot(double q) { return fabs(q) < kPivMin ? -kPivMin : q; }
 //     z_(i-1) = -e z_i / D+_(i-1) upwards, z_(i+1) = -e z_i / D-_(i+1)
 //     downwards.  All lanes walk the same rows (each starts at its own r), so
 //     that the loads are contiguous.
-// Issue of FP64 bounds the eigenvalues (about 14 passes; one shift a pass took
-// 30), memory the vectors of many matrices.  256 x 512^2: 2.33 -> 1.34 ms, 64 x
-// 256^2: 352 -> 290 us, 8 x 1024^2: 1.30 -> 1.07 ms, against one shift a pass, one
-// chain of pivots at a time and a walk from each lane's own r.
+// Its FP64 chains bound the kernel (about 14 passes for the eigenvalues; one shift a
+// pass took 30): at 256 x 512^2 with 1.3 waves a SIMD the VALU is busy 44% of the
+// time, and 3.2 GB of pivots and vectors move at 2.0 TB/s.  256 x 512^2: 2.33 ->
+// 1.34 ms, 64 x 256^2: 352 -> 290 us, 8 x 1024^2: 1.30 -> 1.07 ms, against one shift
+// a pass, one chain of pivots at a time and a walk from each lane's own r.
 // T lies in LDS; the pivots go to global scratch (64 threads of a block on
 // consecutive addresses).
 __global__ __launch_bounds__(64) void k_tri_vectors(TriWs t, const int* mask) {
